@@ -339,6 +339,18 @@ hipError_t launch_dq(const AttnArgs& a, int dqk, hipStream_t s) {
 
 int64_t dq_units_per_head(int64_t nq, int64_t nk, bool causal) { return units_before(nq / 32, (nk + 63) / 64, causal); }
 
+int cu_count() {
+  static int count[64];   // per device
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  int cus = __atomic_load_n(&count[dev], __ATOMIC_RELAXED);
+  if (cus <= 0) {
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 0;
+    __atomic_store_n(&count[dev], cus, __ATOMIC_RELAXED);
+  }
+  return cus;
+}
+
 template <int DQK, int DV>
 static hipError_t bwd_dispatch(const AttnArgs& a0, hipStream_t s) {
   using C = BwdCfg<DQK, DV>;
@@ -346,15 +358,8 @@ static hipError_t bwd_dispatch(const AttnArgs& a0, hipStream_t s) {
   const dim3 grid((unsigned)(nkb * a0.Hkv * a0.B));
   // workgroups of one KV head that run at once: one per compute unit (the
   // kernel's LDS allows one), the units shared by the B Hkv heads
-  static int cu_count[64];   // per device, queried once
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  int cus = __atomic_load_n(&cu_count[dev], __ATOMIC_RELAXED);
-  if (cus <= 0) {
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-      return hipErrorInvalidDevice;
-    __atomic_store_n(&cu_count[dev], cus, __ATOMIC_RELAXED);
-  }
+  const int cus = cu_count();
+  if (cus <= 0) return hipErrorInvalidDevice;
   AttnArgs a = a0;
   const int64_t per_head = cus / (a.B * a.Hkv);
   a.bwd_cohort = (int)(per_head > 1 ? per_head : 1);

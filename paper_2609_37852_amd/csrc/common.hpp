@@ -33,6 +33,12 @@ __device__ __forceinline__ v16f mfma_mx(const v8i& a, const v8i& b, const v16f& 
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, scale_a, 0, scale_b);
 }
 
+// The same with scale bytes SA of scale_a and SB of scale_b.
+template <int SA, int SB>
+__device__ __forceinline__ v16f mfma_mx_sel(const v8i& a, const v8i& b, const v16f& c, int scale_a, int scale_b) {
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, SA, scale_a, SB, scale_b);
+}
+
 // BF16 32x32x16 MFMA with FP32 accumulation: lane l gives 8 BF16 values of
 // row (A) / column (B) l % 32 in the low four dwords of a / b, lane half hf
 // the k values 8 hf .. 8 hf + 7 (the same mapping for both operands, so

@@ -133,6 +133,8 @@ __device__ __forceinline__ SeqLens seq_lens(const AttnArgs& a, int b, int N, int
   return SeqLens{q, k};
 }
 
+// compute units of the current device (queried once per device), 0 on error
+int cu_count();
 hipError_t launch_quantize(const QuantArgs& a, int D, int dtype_bf16, hipStream_t s);
 hipError_t launch_stale_rowsum(const StaleArgs& a, int dout_bf16, int o_bf16, hipStream_t s);
 hipError_t launch_consistent_rowsum(const StaleArgs& a, int o_bf16, hipStream_t s);
