@@ -214,8 +214,8 @@ __device__ __forceinline__ void stage_cols(lds8* st, const BwdLoads<DQK, DV, PDP
   const int lane = threadIdx.x & 63, w = loader_index<DQK, DV>();
   if (w < 0) return;
   const BwdStrides<DQK, DV, PDP> S{N};
-  L.qc.issue_s(st + C::QC_OFF, make_buf(g.qcol, G * S.q()), hi * S.q(), i0, N, lim, w, lane);
-  L.oc.issue_s(st + C::OC_OFF, make_buf(g.ocol, G * S.oc()), hi * S.oc(), i0, N, lim, w, lane);
+  L.qc.issue_s(st + C::QC_OFF, make_buf(g.qcol, G * S.q()), hi * S.q(), i0, lim, w);
+  L.oc.issue_s(st + C::OC_OFF, make_buf(g.ocol, G * S.oc()), hi * S.oc(), i0, lim, w);
   constexpr int NCI = (C::CS_BYTES + 255) / 256;
   for (int k = 0; k < NCI; k++) {
     if ((2 + k) % NWK != w) continue;   // loaders 2, 3, ...: 0 and 1 take the row scales

@@ -161,9 +161,9 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
   kload.init(w, lane);
   vload.init(w, lane);
   auto issue = [&](lds8* st, int j0) __attribute__((always_inline)) {
-    // keys past the sequence are clamped to its last ones (never the padding)
-    kload.issue(st + C::K_OFF, kcode, j0, L.k, w, lane);
-    vload.issue(st + C::V_OFF, vcode, j0, L.k, w, lane);
+    // keys past the sequence read as zero (never the padding)
+    kload.issue(st + C::K_OFF, kcode, j0, L.k, w);
+    vload.issue(st + C::V_OFF, vcode, j0, L.k, w);
     dma_row_scales<DQK, NW, BK>(st + C::KS_OFF, kscale, j0, L.k, w, lane, 0);
     dma_row_scales<DV, NW, BK>(st + C::VS_OFF, vscale, j0, L.k, w, lane, 1);
     if (hot >= 0 && threadIdx.x < BK) {
@@ -194,15 +194,15 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
   int ks[KW], vs[VW];
   float ka = 0.f, ka12 = 0.f;
   auto read_k = [&](const uint8_t* st, int g, int t) __attribute__((always_inline)) {
-    kf[t] = frag_rows_swz<DQK>(st + C::K_OFF, 32 * g + li, t, hf);
-    if (t % 2 == 1 || t == KS - 1) ks[t / 2] = scale_word(st + C::KS_OFF + (32 * g + li) * (DQK / 32), KTAG, t / 2);
+    kf[t] = frag_rows_swz<DQK>(st + C::K_OFF + 32 * g * DQK, li, t, hf);
+    if (t % 2 == 1 || t == KS - 1) ks[t / 2] = scale_word(st + C::KS_OFF + 32 * g * (DQK / 32) + li * (DQK / 32), KTAG, t / 2);
   };
   auto read_v = [&](const uint8_t* st, int g, int t) __attribute__((always_inline)) {
-    vf[t] = frag_rows_swz<DV>(st + C::V_OFF, 32 * g + li, t, hf);
-    if (t % 2 == 1 || t == VS - 1) vs[t / 2] = scale_word(st + C::VS_OFF + (32 * g + li) * (DV / 32), VTAG, t / 2);
+    vf[t] = frag_rows_swz<DV>(st + C::V_OFF + 32 * g * DV, li, t, hf);
+    if (t % 2 == 1 || t == VS - 1) vs[t / 2] = scale_word(st + C::VS_OFF + 32 * g * (DV / 32) + li * (DV / 32), VTAG, t / 2);
   };
   auto read_a = [&](const uint8_t* st, int g) __attribute__((always_inline)) {
-    const float* kh = reinterpret_cast<const float*>(st + C::KH_OFF) + (hf ? BK : 0) + 32 * g + li;
+    const float* kh = reinterpret_cast<const float*>(st + C::KH_OFF) + 32 * g + ((hf ? BK : 0) + li);
     ka = kh[0];
     if constexpr (NH == 3) ka12 = kh[2 * BK];
   };

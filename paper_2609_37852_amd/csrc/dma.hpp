@@ -136,6 +136,9 @@ __device__ __forceinline__ void dma_row_scales_s(lds8* lds, const Buf& b, uint32
 }
 
 // A/B fragment (row `row`, k-step t, half hf) of a swizzled row-major tile.
+// The swizzle repeats every 32 rows: a row 32 g + li is better read as row li
+// of tile + 32 g D, whose constant part the compiler puts in the read's
+// immediate offset.
 template <int D>
 __device__ __forceinline__ v8i frag_rows_swz(const uint8_t* tile, int row, int t, int hf) {
   const int s = swz_row<D>(row), c = 4 * t + hf;
@@ -183,6 +186,7 @@ struct RowLoads {
   // the instructions of one wave are 1024 NWK / D rows apart; the swizzle
   // repeats every 16 rows for every D but 192
   static constexpr bool STRIDED = (1024 * NWK) % D == 0 && ((1024 * NWK) / D) % 16 == 0;
+  static constexpr bool EVEN = NI % NWK == 0;   // every wave issues NS (w < NWK is not known to the compiler)
   uint32_t off[STRIDED ? 1 : NS];   // r D + 16 (swizzled chunk), r the lane's row in the tile
   __device__ __forceinline__ void init(int w, int lane) {
 #pragma unroll
@@ -192,17 +196,14 @@ struct RowLoads {
       off[j] = (uint32_t)(r * D + 16 * (p ^ swz_row<D>(r)));
     }
   }
-  __device__ __forceinline__ void issue(lds8* lds, const uint8_t* code, int i0, int N, int w, int lane) const {
-    if (i0 + ROWS > N) {
-      dma_rows<D, NWK, ROWS>(lds, code, i0, N, w, lane);
-      return;
-    }
+  // Rows at or past N read as zero (the buffer ends there).
+  __device__ __forceinline__ void issue(lds8* lds, const uint8_t* code, int i0, int N, int w) const {
     const Buf b = make_buf(code, (uint32_t)N * D);
     const uint32_t base = (uint32_t)i0 * D;
 #pragma unroll
     for (int j = 0; j < NS; j++) {
       const int k = w + NWK * j;
-      if (k < NI) dma16(b, base + (STRIDED ? off[0] + 1024 * NWK * j : off[j]), lds + 1024 * k);
+      if (EVEN || k < NI) dma16(b, base + (STRIDED ? off[0] + 1024 * NWK * j : off[j]), lds + 1024 * k);
     }
   }
   // Rows of a matrix at byte offset `head` inside buffer b (head: wave-uniform).
@@ -221,7 +222,7 @@ struct RowLoads {
 #pragma unroll
     for (int j = 0; j < NS; j++) {
       const int k = w + NWK * j;
-      if (k < NI) dma16s(b, STRIDED ? off[0] + 1024 * NWK * j : off[j], sb, lds + 1024 * k);
+      if (EVEN || k < NI) dma16s(b, STRIDED ? off[0] + 1024 * NWK * j : off[j], sb, lds + 1024 * k);
     }
   }
 };
@@ -237,60 +238,36 @@ struct ColLoads {
   static constexpr int NI = D * COLS / 1024, NS = (NI + NWK - 1) / NWK;
   static constexpr int CSTEP = 1024 * NWK / COLS;   // channels between a wave's instructions
   static_assert(CSTEP % 16 == 0, "swizzle period");
-  uint32_t off;   // c N + 16 q of the first instruction (q the swizzled chunk)
+  static constexpr bool EVEN = NI % NWK == 0;   // every wave issues NS (w < NWK is not known to the compiler)
+  uint32_t row;   // c N of the first instruction
+  int q16;        // 16 q (q the swizzled chunk)
   int cstride;    // CSTEP N
   __device__ __forceinline__ void init(int w, int lane, int N) {
     const int o = 1024 * w + 16 * lane;
     const int c = o / COLS, p = (o % COLS) / 16;
     const int q = COLS == 64 ? (p ^ swz_col(c)) : (p ^ swz_row<128>(c));
-    off = (uint32_t)(c * N + 16 * q);
+    row = (uint32_t)(c * N);
+    q16 = 16 * q;
     cstride = CSTEP * N;
   }
-  __device__ __forceinline__ void issue(lds8* lds, const uint8_t* code, int i0, int N, int lim, int w,
-                                        int lane) const {
+  // the piece's column, clamped to the last 16 before lim (the same for every instruction)
+  __device__ __forceinline__ int column(int i0, int lim) const { return i0 + q16 < lim - 16 ? i0 + q16 : lim - 16; }
+  __device__ __forceinline__ void issue(lds8* lds, const uint8_t* code, int i0, int N, int lim, int w) const {
     const Buf b = make_buf(code, (uint32_t)D * N);
-    if (i0 + COLS > lim) {
-      // ragged tile: clamp every 16-byte piece into its row
-#pragma unroll
-      for (int j = 0; j < NS; j++) {
-        const int k = w + NWK * j;
-        if (k >= NI) break;
-        const int o = 1024 * k + 16 * lane;
-        const int c = o / COLS, p = (o % COLS) / 16;
-        const int q = COLS == 64 ? (p ^ swz_col(c)) : (p ^ swz_row<128>(c));
-        const int col = i0 + 16 * q < lim - 16 ? i0 + 16 * q : lim - 16;
-        dma16(b, (uint32_t)(c * N + col), lds + 1024 * k);
-      }
-      return;
-    }
-    const uint32_t base = (uint32_t)i0 + off;
+    const uint32_t base = row + (uint32_t)column(i0, lim);
 #pragma unroll
     for (int j = 0; j < NS; j++) {
       const int k = w + NWK * j;
-      if (k < NI) dma16(b, base + (uint32_t)(j * cstride), lds + 1024 * k);
+      if (EVEN || k < NI) dma16(b, base + (uint32_t)(j * cstride), lds + 1024 * k);
     }
   }
   // The same for a matrix at byte offset `head` inside buffer b.
-  __device__ __forceinline__ void issue_s(lds8* lds, const Buf& b, uint32_t head, int i0, int N, int lim, int w,
-                                          int lane) const {
-    if (i0 + COLS > lim) {
-#pragma unroll
-      for (int j = 0; j < NS; j++) {
-        const int k = w + NWK * j;
-        if (k >= NI) break;
-        const int o = 1024 * k + 16 * lane;
-        const int c = o / COLS, p = (o % COLS) / 16;
-        const int q = COLS == 64 ? (p ^ swz_col(c)) : (p ^ swz_row<128>(c));
-        const int col = i0 + 16 * q < lim - 16 ? i0 + 16 * q : lim - 16;
-        dma16s(b, (uint32_t)(c * N + col), head, lds + 1024 * k);
-      }
-      return;
-    }
-    const uint32_t sb = head + (uint32_t)i0;
+  __device__ __forceinline__ void issue_s(lds8* lds, const Buf& b, uint32_t head, int i0, int lim, int w) const {
+    const uint32_t base = row + (uint32_t)column(i0, lim);
 #pragma unroll
     for (int j = 0; j < NS; j++) {
       const int k = w + NWK * j;
-      if (k < NI) dma16s(b, off + (uint32_t)(j * cstride), sb, lds + 1024 * k);
+      if (EVEN || k < NI) dma16s(b, base + (uint32_t)(j * cstride), head, lds + 1024 * k);
     }
   }
 };
