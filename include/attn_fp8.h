@@ -329,7 +329,12 @@ int attn_fp8_delta(const attn_fp8_problem* p, int delta_mode, const attn_fp8_mx*
  * 32-query block x 64-key step at or before the diagonal), the internal delta
  * buffer [B,Hq,N,2], 16-byte per-query records [B,Hq,N] that the main kernel
  * streams with its query tiles, and per-tile packed col scales (Q and dO per
- * 64-query tile, K per 64-key tile).  Returns 0 / negative status. */
+ * 64-query tile, K per 64-key tile); then, for problems with too few key
+ * blocks to fill the chip, FP32 partial sums of dV and dK: each block's query
+ * tiles are split into 2 to 8 parts, added in order at the end.  A workspace
+ * that holds all but the partial sums is accepted too and runs unsplit (the
+ * FP32 sums of dK and dV are then taken in one piece: equal to rounding).
+ * Returns 0 / negative status. */
 int attn_fp8_bwd_workspace_size(const attn_fp8_problem* p, size_t* bytes);
 
 /* Backward (Sec. 2.3; App. B.6.3).  Key-major pass: recompute S, P, dP;
@@ -344,7 +349,7 @@ int attn_fp8_bwd_workspace_size(const attn_fp8_problem* p, size_t* bytes);
  *            computed first per delta_mode, exactly as attn_fp8_delta does.
  *   dq [B,N,Hq,Dqk], dk [B,N,Hkv,Dqk], dv [B,N,Hkv,Dv]: device, grad_dtype,
  *            element strides {b, n, h} in dq_strides / dk_strides / dv_strides.
- *   workspace device, at least attn_fp8_bwd_workspace_size() bytes, 256-byte
+ *   workspace device, attn_fp8_bwd_workspace_size() bytes (see there), 256-byte
  *            aligned; contents on entry are ignored.
  *   rowstats nullable device double [B, Hq, N, 7], zeroed by the caller:
  *            accumulates, per query row and over all keys, sum dS, sum |dS|,
@@ -399,8 +404,10 @@ int attn_fp8_bwd_protected_dp(const attn_fp8_problem* p, const attn_fp8_mx* q,
  * ATTN_FP8_NOALLOC_SCRATCH_BYTES of device memory per device, held from the
  * call that first uses a device until the process ends (its device address
  * is looked up once per device with that device current).
- *   - Problems whose attn_fp8_bwd_workspace_size exceeds the scratch are
- *     rejected with ATTN_FP8_EUNSUPPORTED before anything is launched.
+ *   - Problems whose workspace without partial sums (see
+ *     attn_fp8_bwd_workspace_size) exceeds the scratch are rejected with
+ *     ATTN_FP8_EUNSUPPORTED before anything is launched; one that fits only
+ *     without them runs unsplit.
  *   - The call allocates and frees nothing (no hipMalloc/hipFree, no
  *     allocating library routine).
  *   - All calls on one device share its scratch and leave their contents

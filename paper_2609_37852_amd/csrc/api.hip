@@ -215,7 +215,16 @@ size_t ws_v_bf16_bytes(const attn_fp8_problem* p) {
   return (p->flags & ATTN_FP8_FLAG_PROTECTED_DP) ? round256((size_t)p->batch * p->heads_kv * kv_len(p) * p->dim_v * 2)
                                                  : 0;
 }
-size_t ws_bwd_bytes(const attn_fp8_problem* p) {
+// partial sums of dV and dK of a backward split into n parts (none for 1)
+size_t ws_part_bytes(const attn_fp8_problem* p, int n) {
+  return n > 1 ? round256((size_t)n * p->batch * p->heads_kv * kv_len(p) * (p->dim_qk + p->dim_v) * sizeof(float)) : 0;
+}
+int bwd_parts(const attn_fp8_problem* p) {
+  if (empty(p)) return 1;
+  return afp8::bwd_split(p->batch, p->seqlen, kv_len(p), p->heads_q, p->heads_kv, (int)p->dim_qk, (int)p->dim_v,
+                         p->causal != 0);
+}
+size_t ws_bwd_bytes(const attn_fp8_problem* p) {   // without partial sums
   return ws_units_bytes(p) + ws_exp_bytes(p) + ws_delta_bytes(p) + ws_rows_bytes(p) + ws_tile_cs_bytes(p) +
          ws_tile_kcs_bytes(p) + ws_do_bf16_bytes(p) + ws_v_bf16_bytes(p);
 }
@@ -500,7 +509,7 @@ int attn_fp8_bwd_workspace_size(const attn_fp8_problem* p, size_t* bytes) {
   int rc;
   if ((rc = check_problem(p))) return rc;
   if (!bytes) return fail(ATTN_FP8_EINVAL, "bytes is NULL");
-  *bytes = ws_bwd_bytes(p);
+  *bytes = ws_bwd_bytes(p) + ws_part_bytes(p, bwd_parts(p));
   return ok();
 }
 
@@ -560,6 +569,10 @@ static int bwd_impl(const attn_fp8_problem* p, int delta_mode, const attn_fp8_mx
   uint8_t* tile_kcs = tile_cs + ws_tile_cs_bytes(p);
   uint16_t* do_bf16 = reinterpret_cast<uint16_t*>(tile_kcs + ws_tile_kcs_bytes(p));
   uint16_t* v_bf16 = reinterpret_cast<uint16_t*>(reinterpret_cast<uint8_t*>(do_bf16) + ws_do_bf16_bytes(p));
+  // the split needs its partial sums behind the rest: a workspace without
+  // them (the library's own scratch, a size kept from elsewhere) runs unsplit
+  int nsplit = bwd_parts(p);
+  if (workspace_bytes < need + ws_part_bytes(p, nsplit)) nsplit = 1;
   if (delta_in) {
     delta = const_cast<float*>(delta_in);
   } else if ((rc = launch_delta(p, delta_mode, q, k, v, dout, lse, dout_raw, dout_dtype, dout_strides, o, o_dtype,
@@ -596,6 +609,8 @@ static int bwd_impl(const attn_fp8_problem* p, int delta_mode, const attn_fp8_mx
   a.rows = rows;
   a.tile_cs = tile_cs;
   a.tile_kcs = tile_kcs;
+  a.nsplit = nsplit;
+  a.part = nsplit > 1 ? reinterpret_cast<float*>(ws + need) : nullptr;
   if (pdp) {
     a.pdp = 1;
     a.comp = 0;
@@ -614,6 +629,8 @@ static int bwd_impl(const attn_fp8_problem* p, int delta_mode, const attn_fp8_mx
   if (main_events && (rc = hip_status(hipEventRecord(main_events[0], stream), "event record"))) return rc;
   if ((rc = hip_status(afp8::launch_bwd(a, (int)p->dim_qk, (int)p->dim_v, stream), "bwd"))) return rc;
   if (main_events && (rc = hip_status(hipEventRecord(main_events[1], stream), "event record"))) return rc;
+  if (nsplit > 1 && (rc = hip_status(afp8::launch_bwd_reduce(a, (int)p->dim_qk, (int)p->dim_v, stream), "bwd_reduce")))
+    return rc;
 
   if ((rc = hip_status(afp8::launch_dq(a, (int)p->dim_qk, stream), "dq"))) return rc;
   return ok();

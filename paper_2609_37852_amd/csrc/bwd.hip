@@ -325,6 +325,79 @@ hipError_t launch_pack_bf16(const void* x, int bf16, const int64_t st[3], int64_
   return hipGetLastError();
 }
 
+// dV and dK from the partial sums of a split backward (part-ascending FP32
+// sums; dK times tau, as the unsplit kernel rounds them): four channels per
+// thread, rows past a sequence's keys left unwritten.  HBM- or L2-bound:
+// 4 nsplit + 2 or 4 bytes an element.
+__global__ __launch_bounds__(256) void bwd_reduce_kernel(AttnArgs a, int dqk, int dv) {
+  const int D = dv + dqk, c4n = D / 4;
+  const int64_t rows = a.B * a.Hkv * a.Nk, n4 = rows * c4n, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  const int c = 4 * (int)(i % c4n);
+  const int64_t row = i / c4n, key = row % a.Nk, bk = row / a.Nk, kh = bk % a.Hkv, b = bk / a.Hkv;
+  const SeqLens L = a.causal ? seq_lens<true>(a, (int)b, (int)a.N, (int)a.Nk) : seq_lens<false>(a, (int)b, (int)a.N, (int)a.Nk);
+  if (key >= L.k) return;
+  float4 v = reinterpret_cast<const float4*>(a.part)[i];
+  for (int s = 1; s < a.nsplit; s++) {
+    const float4 x = reinterpret_cast<const float4*>(a.part)[i + s * n4];
+    v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+  }
+  const bool isk = c >= dv;
+  if (isk) { v.x *= a.tau; v.y *= a.tau; v.z *= a.tau; v.w *= a.tau; }
+  const int64_t* st = isk ? a.dks : a.dvs;
+  const int64_t o = b * st[0] + key * st[1] + kh * st[2] + (isk ? c - dv : c);
+  void* out = isk ? a.dk : a.dv;
+  if (a.grad_bf16) {
+    uint2 w;
+    w.x = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
+    w.y = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
+    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + o) = w;
+  } else {
+    *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o) = v;
+  }
+}
+
+hipError_t launch_bwd_reduce(const AttnArgs& a, int dqk, int dv, hipStream_t s) {
+  const int64_t n4 = a.B * a.Hkv * a.Nk * ((dqk + dv) / 4);
+  hipLaunchKernelGGL(bwd_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, a, dqk, dv);
+  return hipGetLastError();
+}
+
+// A key block's workgroup walks G heads x its query tiles one after another,
+// so a problem with few key blocks leaves compute units idle while its longest
+// block runs.  Splitting the tiles into n parts shortens that to 1 / n, at the
+// price of n FP32 partial sums written and read again and one more launch.
+// The model, for the 256 compute units of the whole chip: a tile step takes
+// 1.75 us at dqk + dv = 256 (scaled with it); without the mask all parts are
+// alike and run in rounds of one per compute unit, under it the launch ends no
+// sooner than its longest part and than its steps spread evenly; partial sums
+// move at 4 TB/s; the added launch and its pass take 8 us.  Backward call unsplit / split, 16 / 4
+// heads of 128, one sequence, causal: 512 tokens 76 / 43 us, 1024 128 / 55,
+// 2080 243 / 117, 4096 445 / 204, 8192 918 / 631; d = 256, 8 / 2 heads, 2048
+// tokens 320 / 128; 4 x 8192 tokens are not split.
+int bwd_split(int64_t B, int64_t N, int64_t Nk, int64_t Hq, int64_t Hkv, int dqk, int dv, bool causal) {
+  constexpr int64_t CUS = 256;
+  const int64_t bkb = dqk + dv > 256 ? 64 : 128, nkb = (Nk + bkb - 1) / bkb, nqt = (N + 63) / 64, G = Hq / Hkv;
+  const double step = 1.75 * (dqk + dv) / 256;
+  double total = 0;                                  // steps of all workgroups
+  for (int64_t j = 0; j < nkb; j++) total += causal ? nqt - j * bkb / 64 : nqt;
+  total *= (double)(B * Hq);
+  const double per_part = (double)(B * Hkv * Nk) * (dqk + dv) * 8 / 4e6;   // us
+  int best = 1;
+  double t_best = 0;   // the time to beat: that without a split, less a fifth for the model's own error
+  for (int n = 1; n <= 8 && n <= nqt; n++) {
+    const double longest = (double)(G * ((nqt + n - 1) / n)), spread = total / CUS;
+    const int64_t rounds = (nkb * B * Hkv * n + CUS - 1) / CUS;
+    const double steps = causal ? (longest > spread ? longest : spread) : longest * rounds;
+    const double t = steps * step + (n > 1 ? 8 + n * per_part : 0);
+    if (n == 1 || t < t_best) {
+      best = n;
+      t_best = n == 1 ? 0.8 * t : t;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_dq(const AttnArgs& a, int dqk, hipStream_t s) {
   const dim3 grid((unsigned)((a.N / 32 + 3) / 4 * a.Hq * a.B));
   switch (dqk) {
@@ -355,13 +428,13 @@ template <int DQK, int DV>
 static hipError_t bwd_dispatch(const AttnArgs& a0, hipStream_t s) {
   using C = BwdCfg<DQK, DV>;
   const int64_t nkb = (a0.Nk + C::BKB - 1) / C::BKB;
-  const dim3 grid((unsigned)(nkb * a0.Hkv * a0.B));
-  // workgroups of one KV head that run at once: one per compute unit (the
-  // kernel's LDS allows one), the units shared by the B Hkv heads
+  const dim3 grid((unsigned)(nkb * a0.Hkv * a0.B * a0.nsplit));
+  // workgroups of one KV head and part that run at once: one per compute unit
+  // (the kernel's LDS allows one), the units shared by the B Hkv heads
   const int cus = cu_count();
   if (cus <= 0) return hipErrorInvalidDevice;
   AttnArgs a = a0;
-  const int64_t per_head = cus / (a.B * a.Hkv);
+  const int64_t per_head = cus / (a.B * a.Hkv * a.nsplit);
   a.bwd_cohort = (int)(per_head > 1 ? per_head : 1);
   if (a.pdp) return a.causal ? launch_bwd_main<true, 4>(a, DQK, DV, grid, s) : launch_bwd_main<false, 4>(a, DQK, DV, grid, s);
   if (a.iso3) return a.causal ? launch_bwd_main<true, 8>(a, DQK, DV, grid, s) : launch_bwd_main<false, 8>(a, DQK, DV, grid, s);

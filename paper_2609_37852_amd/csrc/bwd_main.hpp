@@ -326,7 +326,9 @@ __global__ __launch_bounds__((BwdCfg<DQK, DV>::NT)) void bwd_kernel(AttnArgs a) 
   // mod 16, hence one XCD and its L2 when B * Hkv % 8 == 0)
   // (with sequences of their own lengths the groups rotate over the XCDs
   // from one slot to the next, as in query_major_coord)
-  const int GI = (int)(a.B * a.Hkv), slot = (int)blockIdx.x / GI;
+  // (split launches: a slot's parts follow one another, each of all groups)
+  const int GI = (int)(a.B * a.Hkv), NSP = a.nsplit, slot = (int)blockIdx.x / (GI * NSP);
+  const int sp = (int)blockIdx.x / GI - slot * NSP;
   const KeyBlock kbk = key_block_of(slot, (Nk + BKB - 1) / BKB, a.bwd_cohort);
   const int kb0 = kbk.kb * BKB;
   const bool up = kbk.up;
@@ -424,8 +426,10 @@ __global__ __launch_bounds__((BwdCfg<DQK, DV>::NT)) void bwd_kernel(AttnArgs a) 
 #pragma unroll
     for (int r = 0; r < 16; r++) acc[i][r] = 0.f;
 
+  // this part's query tiles: steps r0 .. r1 - 1 along the sequence
   const int nqt = (L.q + BQ - 1) / BQ, qt0 = causal ? kb0 / BQ : 0, nq = nqt - qt0;
-  const int total = G * nq;                     // 0 only for a sequence without queries
+  const int r0 = nq * sp / NSP, r1 = nq * (sp + 1) / NSP;
+  const int total = G * (r1 - r0);              // 0 for a sequence without queries, or more parts than tiles
   const size_t bh0 = (size_t)b * Hq + (size_t)kh * G;   // first query head of the group
   const int nks = (Nk + 63) / 64;               // 64-key steps of the dQ units
   const int64_t units_per_head = units_before(N / 32, nks, causal);
@@ -801,7 +805,7 @@ __global__ __launch_bounds__((BwdCfg<DQK, DV>::NT)) void bwd_kernel(AttnArgs a) 
 
   // prologue: rows of tiles 0 and 1, cols of tile 0; S, dP, P, dS of tile 0
   // (none without queries: the key gradients are then zero)
-  const TilePos p0 = TilePos{0, 0};
+  const TilePos p0 = TilePos{0, r0};
   if (total > 0) {
     stage_rows<DQK, DV, PDP>((lds8*)rA, ld, grp, G, p0.hi, q0_of(p0), N, L.q);
     stage_cols<DQK, DV, PDP>((lds8*)cA, ld, grp, G, p0.hi, q0_of(p0), N, L.q);
@@ -831,6 +835,22 @@ __global__ __launch_bounds__((BwdCfg<DQK, DV>::NT)) void bwd_kernel(AttnArgs a) 
   }
 
   if (!live) return;
+  if (NSP > 1) {
+    // this part's FP32 sums; bwd_reduce_kernel adds the parts and rounds
+    float* pt = a.part + ((size_t)sp * GI + bhk) * Nk * (DV + DQK) + (qs ? DV : 0) + li;
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+      float* row = pt + (size_t)(kw0 + 8 * (r >> 2) + 4 * hf + (r & 3)) * (DV + DQK);
+      if (qs == 0) {
+#pragma unroll
+        for (int i = 0; i < CV; i++) row[32 * i] = acc[i][r];
+      } else {
+#pragma unroll
+        for (int i = 0; i < CK; i++) row[32 * i] = acc[i][r];
+      }
+    }
+    return;
+  }
   // dV (first half) or dK times tau (second half): lane holds channel
   // 32 i + li, keys kw0 + 8 (r/4) + 4 hf + r % 4
 #pragma unroll

@@ -99,6 +99,8 @@ struct AttnArgs {
   void* dk; int64_t dks[3];
   void* dv; int64_t dvs[3];
   int grad_bf16;
+  int nsplit;                          // backward: parts of a key block's query tiles (set at launch)
+  float* part;                         // with nsplit > 1: [nsplit, B, Hkv, Nk, Dv + Dqk] partial sums of dV, dK (workspace)
   int bwd_cohort;                      // backward: workgroups of one KV head that run at once (set at launch)
   double* rowstats;                    // nullable [B,Hq,N,kRowStats]
   void* cast_dump;                     // nullable, with rowstats: pre-cast P, dS and their codes
@@ -143,6 +145,9 @@ hipError_t launch_fwd(const AttnArgs& a, int dqk, int dv, hipStream_t s);
 hipError_t launch_delta_matching(const AttnArgs& a, int dqk, int dv, hipStream_t s);
 hipError_t launch_bwd_prep(const AttnArgs& a, int dqk, int dv, hipStream_t s);
 hipError_t launch_bwd(const AttnArgs& a, int dqk, int dv, hipStream_t s);
+// parts that launch_bwd best splits each key block's query tiles into (1: none), with a.part
+int bwd_split(int64_t B, int64_t N, int64_t Nk, int64_t Hq, int64_t Hkv, int dqk, int dv, bool causal);
+hipError_t launch_bwd_reduce(const AttnArgs& a, int dqk, int dv, hipStream_t s);
 hipError_t launch_dq(const AttnArgs& a, int dqk, hipStream_t s);
 hipError_t launch_pack_bf16(const void* x, int bf16, const int64_t st[3], int64_t B, int64_t N, int64_t H, int D,
                             const int32_t* lens, uint16_t* out, hipStream_t s);
