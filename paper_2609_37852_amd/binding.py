@@ -103,12 +103,18 @@ def _check(fn, rc):
         raise AttnFp8Error(fn, rc, last_error())
 
 
+# Marshalling takes the short way everywhere (plain integers for pointers, the
+# raw stream handle, one stride query per tensor): the smallest calls run as
+# fast as the host issues them.
+
+
 def _stream(device=None):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    i = device.index if device is not None else None
+    return torch._C._cuda_getCurrentRawStream(i if i is not None else torch.cuda.current_device())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _dtype_code(dt):
@@ -120,8 +126,9 @@ def _dtype_code(dt):
 
 
 def _strides_bnh(t):
-    assert t.dim() == 4 and t.stride(3) == 1, "expected [B, N, H, D] with contiguous channels"
-    return _I64x3(t.stride(0), t.stride(1), t.stride(2))
+    st = t.stride()
+    assert len(st) == 4 and st[3] == 1, "expected [B, N, H, D] with contiguous channels"
+    return _I64x3(st[0], st[1], st[2])
 
 
 @dataclass
@@ -154,7 +161,7 @@ class Problem:
                 "seqlens: contiguous int32 [batch] tensors"
         return _Problem(self.batch, self.seqlen, self.heads_q, self.heads_kv, self.dim_qk, self.dim_v,
                         self.causal, self.softmax_scale, self.seqlen_kv, self.flags,
-                        _ptr(self.seqlens_q).value, _ptr(self.seqlens_kv).value, _ptr(self.cast_dump).value)
+                        _ptr(self.seqlens_q), _ptr(self.seqlens_kv), _ptr(self.cast_dump))
 
     def cast_dump_bytes(self) -> int:
         s = self.batch * self.heads_q * self.seqlen * self.nk
@@ -183,19 +190,19 @@ class MX:
     channel_amax: torch.Tensor | None = None
 
     def c(self):
-        return _MX(*(t.data_ptr() if t is not None else None
-                     for t in (self.code_row, self.scale_row, self.code_col, self.scale_col, self.channel_amax)))
+        return _MX(_ptr(self.code_row), _ptr(self.scale_row), _ptr(self.code_col), _ptr(self.scale_col),
+                   _ptr(self.channel_amax))
 
     @staticmethod
     def empty(B, N, H, D, device, which=QUANT_BOTH, amax=True):
-        u8 = dict(dtype=torch.uint8, device=device)
         row = which & QUANT_ROW
         col = which & QUANT_COL
-        return MX(torch.empty((B, H, N, D), **u8) if row else None,
-                  torch.empty((B, H, N, D // 32), **u8) if row else None,
-                  torch.empty((B, H, D, N), **u8) if col else None,
-                  torch.empty((B, H, D, N // 32), **u8) if col else None,
-                  torch.empty((B, H, D), dtype=torch.float32, device=device) if (amax and col) else None)
+        u8, empty = torch.uint8, torch.empty
+        return MX(empty((B, H, N, D), dtype=u8, device=device) if row else None,
+                  empty((B, H, N, D // 32), dtype=u8, device=device) if row else None,
+                  empty((B, H, D, N), dtype=u8, device=device) if col else None,
+                  empty((B, H, D, N // 32), dtype=u8, device=device) if col else None,
+                  empty((B, H, D), dtype=torch.float32, device=device) if (amax and col) else None)
 
 
 def attn_fp8_quantize(x: torch.Tensor, which: int = QUANT_BOTH, nonfinite: torch.Tensor | None = None,
@@ -236,8 +243,8 @@ def attn_fp8_quantize_producer(x: torch.Tensor, prescale: float = 1.0, center: b
     mean = torch.empty((B, H, D), dtype=torch.float32, device=x.device) if center else None
     if seqlens is not None:
         assert seqlens.dtype == torch.int32 and seqlens.shape == (B,)
-    opt = _Producer(float(prescale), int(bool(center)), _ptr(mean).value, _ptr(rms_gain).value, float(rms_eps),
-                    _ptr(rope).value, int(rope_lo), int(rope_dim), _ptr(seqlens).value)
+    opt = _Producer(float(prescale), int(bool(center)), _ptr(mean), _ptr(rms_gain), float(rms_eps),
+                    _ptr(rope), int(rope_lo), int(rope_dim), _ptr(seqlens))
     need = ctypes.c_size_t(0)
     _check("attn_fp8_producer_workspace_size",
            lib().attn_fp8_producer_workspace_size(B, N, H, D, ctypes.byref(opt), ctypes.byref(need)))
@@ -304,9 +311,8 @@ def attn_fp8_bwd(p: Problem, mode: int, q: MX, k: MX, v: MX, dout: MX, lse, dout
         dv = torch.empty((p.batch, p.nk, p.heads_kv, p.dim_v), dtype=grad_dtype, device=dev)
     else:
         dq, dk, dv = out
-    ws_bytes = attn_fp8_bwd_workspace_size(p)
     if workspace is None:
-        workspace = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=dev)
+        workspace = torch.empty(max(attn_fp8_bwd_workspace_size(p), 256), dtype=torch.uint8, device=dev)
     rs = torch.zeros((p.batch, p.heads_q, p.seqlen, ROWSTATS), dtype=torch.float64, device=dev) if rowstats else None
     pc = p.c()
     mxs = [m.c() for m in (q, k, v, dout)]
@@ -334,9 +340,8 @@ def attn_fp8_bwd_protected_dp(p: Problem, q: MX, k: MX, dout: MX, lse, dout_raw,
         dv = torch.empty((p.batch, p.nk, p.heads_kv, p.dim_v), dtype=grad_dtype, device=dev)
     else:
         dq, dk, dv = out
-    ws_bytes = attn_fp8_bwd_workspace_size(p)
     if workspace is None:
-        workspace = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=dev)
+        workspace = torch.empty(max(attn_fp8_bwd_workspace_size(p), 256), dtype=torch.uint8, device=dev)
     rs = torch.zeros((p.batch, p.heads_q, p.seqlen, ROWSTATS), dtype=torch.float64, device=dev) if rowstats else None
     pc = p.c()
     mxs = [m.c() for m in (q, k, dout)]

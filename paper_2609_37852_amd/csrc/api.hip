@@ -65,18 +65,18 @@ int check_ptr(const char* name, const void* p) {
   return ATTN_FP8_OK;
 }
 
+int check_field(const char* name, const char* field, const void* p) {
+  if (p && aligned16(p)) return ATTN_FP8_OK;
+  return check_ptr((std::string(name) + field).c_str(), p);
+}
+
 int check_mx(const char* name, const attn_fp8_mx* m, bool row, bool col) {
   if (!m) return fail(ATTN_FP8_EINVAL, "%s: operand pointer is NULL", name);
-  std::string n(name);
   int rc;
-  if (row) {
-    if ((rc = check_ptr((n + ".code_row").c_str(), m->code_row))) return rc;
-    if ((rc = check_ptr((n + ".scale_row").c_str(), m->scale_row))) return rc;
-  }
-  if (col) {
-    if ((rc = check_ptr((n + ".code_col").c_str(), m->code_col))) return rc;
-    if ((rc = check_ptr((n + ".scale_col").c_str(), m->scale_col))) return rc;
-  }
+  if (row && ((rc = check_field(name, ".code_row", m->code_row)) || (rc = check_field(name, ".scale_row", m->scale_row))))
+    return rc;
+  if (col && ((rc = check_field(name, ".code_col", m->code_col)) || (rc = check_field(name, ".scale_col", m->scale_col))))
+    return rc;
   return ATTN_FP8_OK;
 }
 
