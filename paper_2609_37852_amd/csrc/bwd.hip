@@ -238,8 +238,7 @@ __global__ __launch_bounds__(256, DQK <= 128 ? 4 : 1) void dq_kernel(AttnArgs a)
                          (int)op[s].hi.x, (int)op[s].hi.y, (int)op[s].hi.z, (int)op[s].hi.w};
 #pragma unroll
       for (int i = 0; i < CQ; i++) {
-        const int ch = 32 * i + li;
-        acc[i] = mfma_mx(af, frag_cols_swz(kt, ch, hf), acc[i], (int)op[s].e, kt[KT + 2 * ch + hf]);
+        acc[i] = mfma_mx(af, frag_cols_swz(kt + 32 * i * 64, li, hf), acc[i], (int)op[s].e, (kt + KT + 64 * i)[2 * li + hf]);
       }
     }
   };

@@ -659,9 +659,9 @@ __global__ __launch_bounds__((BwdCfg<DQK, DV>::NT)) void bwd_kernel(AttnArgs a) 
       if (m < NSD) {
         const int t = sd_t(m);
         if (sd_is_s(m)) {
-          r.a = frag_rows_swz<DQK>(Q, qrow, t, hf);
+          r.a = frag_rows_swz<DQK>(Q + 32 * qs * DQK, li, t, hf);
           r.b = kfrag(t);
-          r.sa = Qs[qrow * (DQK / 32) + 2 * t + hf];
+          r.sa = (Qs + 2 * t)[qrow * (DQK / 32) + hf];
           r.sb = ksc[t];
         } else if constexpr (PDP) {
           // BF16 fragments of channels 16 t + 8 hf .. + 7 of the query's dO
@@ -674,17 +674,17 @@ __global__ __launch_bounds__((BwdCfg<DQK, DV>::NT)) void bwd_kernel(AttnArgs a) 
           r.sa = 0;
           r.sb = 0;
         } else {
-          r.a = frag_rows_swz<DV>(O, qrow, t, hf);
+          r.a = frag_rows_swz<DV>(O + 32 * qs * DV, li, t, hf);
           r.b = vfrag(t);
-          r.sa = Os[qrow * (DV / 32) + 2 * t + hf];
+          r.sa = (Os + 2 * t)[qrow * (DV / 32) + hf];
           r.sb = vsc[t];
         }
       } else {
-        const int ch = 32 * (m - NSD) + li;
+        const int ch0 = 32 * (m - NSD);
         r.a = A;
-        r.b = frag_cols_chunks(Bt, ch, clo, chi);
+        r.b = frag_cols_chunks(Bt + ch0 * 64, li, clo, chi);
         r.sa = ascale;
-        r.sb = Bs[ch * 2 + sbk];
+        r.sb = (Bs + 2 * ch0)[li * 2 + sbk];
       }
       return r;
     };
