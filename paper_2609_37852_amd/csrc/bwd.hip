@@ -378,9 +378,8 @@ int bwd_split(int64_t B, int64_t N, int64_t Nk, int64_t Hq, int64_t Hkv, int dqk
   constexpr int64_t CUS = 256;
   const int64_t bkb = dqk + dv > 256 ? 64 : 128, nkb = (Nk + bkb - 1) / bkb, nqt = (N + 63) / 64, G = Hq / Hkv;
   const double step = 1.75 * (dqk + dv) / 256;
-  double total = 0;                                  // steps of all workgroups
-  for (int64_t j = 0; j < nkb; j++) total += causal ? nqt - j * bkb / 64 : nqt;
-  total *= (double)(B * Hq);
+  // steps of all workgroups: nqt of each key block, less those before its diagonal
+  const double total = (double)(B * Hq) * ((double)nkb * nqt - (causal ? (double)(bkb / 64) * nkb * (nkb - 1) / 2 : 0.0));
   const double per_part = (double)(B * Hkv * Nk) * (dqk + dv) * 8 / 4e6;   // us
   int best = 1;
   double t_best = 0;   // the time to beat: that without a split, less a fifth for the model's own error

@@ -77,19 +77,6 @@ __device__ __forceinline__ void lds_sync() {
   asm volatile("" ::: "memory");
 }
 
-// Row-major code tile [ROWS][D] (rows i0.., clamped to the sequence) into
-// LDS, swizzled; wave w issues instructions w, w + NWK, ...
-template <int D, int NWK, int ROWS = 64>
-__device__ __forceinline__ void dma_rows(lds8* lds, const uint8_t* code, int i0, int N, int w, int lane) {
-  constexpr int NI = ROWS * D / 1024;
-  const Buf b = make_buf(code, (uint32_t)N * D);
-  for (int k = w; k < NI; k += NWK) {
-    const int off = 1024 * k + 16 * lane;
-    const int r = off / D, p = (off % D) / 16;
-    const int row = i0 + r < N ? i0 + r : N - 1;
-    dma16(b, (uint32_t)(row * D + 16 * (p ^ swz_row<D>(r))), lds + 1024 * k);
-  }
-}
 // Col-copy code tile: channels [0, D), queries [i0, i0 + 64) of a [D][N]
 // matrix, clamped to the first lim (<= N, >= 16) -> [D][64].
 template <int D, int NWK>
@@ -176,8 +163,7 @@ __device__ __forceinline__ v8i frag_cols_chunks(const uint8_t* tile, int ch, int
 // Precomputed plans for the tile loads of one wave: the lane's byte offset in
 // the source matrix for its first load instruction (k = w); the later ones
 // (k = w + NWK j) sit a fixed stride further wherever the swizzle repeats
-// with that stride, so a whole tile costs one address add per load.  A tile
-// that reaches past the sequence end takes the clamping loaders above.
+// with that stride, so a whole tile costs one address add per load.
 //
 // Row tile: rows [i0, i0 + ROWS) of a [N][D] code matrix -> LDS [ROWS][D].
 template <int D, int NWK, int ROWS>
