@@ -90,8 +90,8 @@ typedef enum {
                                        (an opt-in refinement, not from the paper): the
                                        pre-cast row sums then meet 1e-5 max_j |dS_ij|
                                        down to max|dS| / max P|dP| = 2^-31 (2^-5 with
-                                       the plain formation), for about 17 % more time
-                                       in the correction pass and 8 % in the main
+                                       the plain formation), for about 20 % more time
+                                       in the correction pass and 7 % in the main
                                        backward kernel (d = 128, 8K)                  */
 } attn_fp8_delta_mode;
 
