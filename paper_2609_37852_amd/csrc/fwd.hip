@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
 #pragma unroll
     for (int r = 0; r < 16; r++) oacc[cb][r] = 0.f;
   float M = -__builtin_inff();
-  float ls[2] = {0.f, 0.f};                   // the lane's keys' exponentials, in two interleaved sums
+  float lsum = 0.f;                           // the lane's keys' exponentials, keys ascending
   const float c = a.c;
   // key tiles up to the block's diagonal, or over all keys; the first nfull
   // hold only keys that every query of the workgroup sees
@@ -289,8 +289,7 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
       const float df = __builtin_fmaxf(M - mnew, -300.f);  // M is -inf at first
       const int d = (int)df;                              // 0 for lanes whose maximum did not move
       const float alpha = d < -126 ? 0.f : exp2i(d);
-      ls[0] *= alpha;
-      ls[1] *= alpha;
+      lsum *= alpha;
 #pragma unroll
       for (int cb = 0; cb < CB; cb++)
 #pragma unroll
@@ -324,14 +323,14 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
     }
     const int j = i - LAG;
     if (j >= 0 && j < 16) {
-      ls[0] += p[2 * j];
-      ls[1] += p[2 * j + 1];
+      lsum += p[2 * j];
+      lsum += p[2 * j + 1];
       const float sc = sc2[j >> 3];
       v2s w2 = (j & 1) ? __builtin_bit_cast(v2s, cd[j >> 1]) : __builtin_bit_cast(v2s, p[2 * j]);
       if (j & 1) w2 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w2, p[2 * j], p[2 * j + 1], sc, true);
       else w2 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w2, p[2 * j], p[2 * j + 1], sc, false);
       cd[j >> 1] = __builtin_bit_cast(int, w2);
-      asm volatile("" : "+v"(ls[0]), "+v"(ls[1]), "+v"(cd[j >> 1]));
+      asm volatile("" : "+v"(lsum), "+v"(cd[j >> 1]));
     }
   };
   v8i npfr;
@@ -483,7 +482,6 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
     }
   }
   if (!live) return;
-  const float lsum = ls[0] + ls[1];
   const float l = lsum + partner(lsum);
   const float inv = 1.0f / l;
   // lane (query qi, half hf) holds channels 32 cb + 8 (r/4) + 4 hf + r % 4
