@@ -140,8 +140,8 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
       if (hot >= 0) qv12[u] = row_value<DQK>(a.q_code, a.q_scale, (int64_t)row, hf ? hots[2] : hots[1]);
     }
   }
-  // this lane's share (its 16 keys of every group) of each row's sums
-  double num[QB] = {}, den[QB] = {};
+  // each row's sums over the groups: of P dP in lanes < 32, of P in lanes >= 32
+  double sum[QB] = {};
 
   const uint8_t* kcode = a.k_code + bhk * Nk * DQK;
   const uint8_t* kscale = a.k_scale + bhk * Nk * (DQK / 32);
@@ -238,35 +238,39 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
   };
 
   // Vector work of a unit: P (mask: the group holding the wave's diagonal,
-  // keys after the query), then its share of the sums of P dP and P.  The
-  // lane holds keys 8 (r/4) + 4 hf + r % 4 of the group, one query; two
-  // interleaved partial sums of each (four in FP64).  Element r's
-  // probability is item r (or r + its position below), its product four
-  // elements later, so that the last MFMA has finished before dP is read.
+  // keys after the query), then the group's sums of P dP and P.  The lane
+  // holds keys 8 (r/4) + 4 hf + r % 4 of the group, one query, and sums them
+  // in this order (FP32, COMP: FP64); one exchange then gives lanes < 32 both
+  // halves' sums of P dP, lanes >= 32 those of P, whose total each adds to
+  // its FP64 sum.
   float p[16];
-  float pn[2], pd[2];
-  double qn[2], qd[2];
+  float pn, pd;
+  double qn, qd;
   auto elem_p = [&](int r, const v16f& s, bool diag) __attribute__((always_inline)) {
     p[r] = bwd_prob(s[r], a.c);
     if (diag) p[r] = (8 * (r >> 2) + 4 * hf + (r & 3)) > li ? 0.f : p[r];
-    if constexpr (COMP) qd[r & 1] = r < 2 ? (double)p[r] : qd[r & 1] + (double)p[r];
-    else pd[r & 1] = r < 2 ? p[r] : pd[r & 1] + p[r];
+    if constexpr (COMP) qd = r == 0 ? (double)p[r] : qd + (double)p[r];
+    else pd = r == 0 ? p[r] : pd + p[r];
   };
   auto elem_n = [&](int r, const v16f& dp) __attribute__((always_inline)) {
-    if constexpr (COMP) qn[r & 1] = r < 2 ? (double)p[r] * (double)dp[r] : __builtin_fma((double)p[r], (double)dp[r], qn[r & 1]);   // exact products
-    else pn[r & 1] = r < 2 ? p[r] * dp[r] : __builtin_fmaf(p[r], dp[r], pn[r & 1]);
+    if constexpr (COMP) qn = r == 0 ? (double)p[r] * (double)dp[r] : __builtin_fma((double)p[r], (double)dp[r], qn);   // exact products
+    else pn = r == 0 ? p[r] * dp[r] : __builtin_fmaf(p[r], dp[r], pn);
   };
   auto add_sums = [&](int u) __attribute__((always_inline)) {
     if constexpr (COMP) {
-      num[u] += qn[0] + qn[1];
-      den[u] += qd[0] + qd[1];
+      const uint64_t a = __builtin_bit_cast(uint64_t, qn), b = __builtin_bit_cast(uint64_t, qd);
+      const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+      const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+      sum[u] += __builtin_bit_cast(double, (uint64_t)lo[0] | (uint64_t)hi[0] << 32) +
+                __builtin_bit_cast(double, (uint64_t)lo[1] | (uint64_t)hi[1] << 32);
     } else {
-      num[u] += (double)(pn[0] + pn[1]);
-      den[u] += (double)(pd[0] + pd[1]);
+      const Pair t = permlane32_swap(pn, pd);
+      sum[u] += (double)(t.lo + t.hi);
     }
-    asm volatile("" : "+v"(num[u]), "+v"(den[u]));   // here, not after later units
+    asm volatile("" : "+v"(sum[u]));   // here, not after later units
   };
-  // items 0 .. 35 of the vector work, in order: P of element i, product of element i - 4
+  // items 0 .. 19 of the vector work, in order: P of element i, product of
+  // element i - 4 (so that the last MFMA has finished before dP is read)
   constexpr int LAG = 4, NI = 16 + LAG;
   auto item = [&](int i, const v16f& s, const v16f& dp) __attribute__((always_inline)) {
     if (i < 16) elem_p(i, s, false);
@@ -274,8 +278,8 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
   };
 
   auto pin = [&]() __attribute__((always_inline)) {
-    if constexpr (COMP) asm volatile("" : "+v"(qn[0]), "+v"(qn[1]), "+v"(qd[0]), "+v"(qd[1]));
-    else asm volatile("" : "+v"(pn[0]), "+v"(pn[1]), "+v"(pd[0]), "+v"(pd[1]));
+    if constexpr (COMP) asm volatile("" : "+v"(qn), "+v"(qd));
+    else asm volatile("" : "+v"(pn), "+v"(pd));
   };
 
   v16f s0, dp0, s1, dp1;
@@ -323,7 +327,7 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
       if constexpr (QB == 2) {
         // at the first unit of all there is no vector work yet: its items run on zeros (P = 1 of zero scores, dP zero) and are dropped
         phase(0, s0, dp0, 1, s1, dp1, false, src, gn);
-        if (first && g == 0) num[1] = den[1] = 0.0;
+        if (first && g == 0) sum[1] = 0.0;
         if (last) turn(cur, nxt, t);
         phase(1, s1, dp1, 0, s0, dp0, true, src, gn);
       } else {
@@ -332,7 +336,7 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
           phase(0, s1, dp1, 0, s0, dp0, true, src, gn);
         } else {
           phase(0, s0, dp0, 0, s1, dp1, true, src, gn);
-          if (first && g == 0) num[0] = den[0] = 0.0;
+          if (first && g == 0) sum[0] = 0.0;
         }
       }
     }
@@ -383,7 +387,7 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
 #pragma unroll
   for (int u = 0; u < QB; u++) {
     const int qi = q0 + 32 * u + li;
-    const double n = num[u] + __shfl_xor(num[u], 32), m = den[u] + __shfl_xor(den[u], 32);
+    const double n = sum[u], m = __shfl_xor(sum[u], 32);   // in lanes < 32
     if (q0 + 32 * u >= L.q || hf != 0) continue;
     const double d = m > 0.0 ? n / m : 0.0;
     const float hi = (float)d;
