@@ -109,6 +109,10 @@ def _check(fn, rc):
 
 
 def _stream(device=None):
+    """Raw handle of the current stream of `device` (a GPU: nothing else guards
+    the library from the address of a host tensor), or of the current GPU."""
+    if device is not None and device.type != "cuda":
+        raise ValueError(f"expected tensors on a GPU, but got device {device}")
     i = device.index if device is not None else None
     return torch._C._cuda_getCurrentRawStream(i if i is not None else torch.cuda.current_device())
 

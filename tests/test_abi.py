@@ -315,3 +315,40 @@ def test_isolate3_combinations():
                         *[ctypes.c_void_p(4096)] * 3, 1, st, st, st, ctypes.c_void_p(4096), 1, None, None,
                         None)
     assert rc == -2 and "isolated" in pk.last_error()
+
+
+def test_tensors_off_the_gpu_are_refused(monkeypatch):
+    """Every entry point that launches work refuses operands that are not on a
+    GPU before it calls the library (whose checks see only addresses)."""
+    import torch
+    real = pk.lib()
+
+    class HostOnly:   # the library without the functions that launch
+        attn_fp8_bwd_workspace_size = real.attn_fp8_bwd_workspace_size
+        attn_fp8_producer_workspace_size = real.attn_fp8_producer_workspace_size
+
+        def __getattr__(self, name):
+            def launch(*a):
+                pytest.fail(f"{name} was called with host addresses")
+            return launch
+
+    monkeypatch.setattr(bd, "lib", HostOnly)
+    B, N, H, D = 1, 32, 2, 64
+    x, lse = torch.zeros((B, N, H, D)), torch.zeros((B, H, N))
+    m = pk.MX.empty(B, N, H, D, "cpu")
+    p = pk.Problem(B, N, H, H, D, D, 0.125)
+    pp = pk.Problem(B, N, H, H, D, D, 0.125, flags=pk.FLAG_PROTECTED_DP)
+    calls = [lambda: pk.attn_fp8_quantize(x),
+             lambda: pk.attn_fp8_quantize_producer(x, center=True),
+             lambda: pk.attn_fp8_fwd(p, m, m, m),
+             lambda: pk.attn_fp8_delta(p, pk.DELTA_MATCHING, m, m, m, m, lse=lse),
+             lambda: pk.attn_fp8_delta(p, pk.DELTA_STALE_ROWSUM, dout_raw=x, o=x),
+             lambda: pk.attn_fp8_bwd(p, pk.DELTA_MATCHING, m, m, m, m, lse),
+             lambda: pk.attn_fp8_bwd_noalloc(p, pk.DELTA_MATCHING, m, m, m, m, lse),
+             lambda: pk.attn_fp8_bwd_protected_dp(pp, m, m, m, lse, x, x, x)]
+    for call in calls:
+        with pytest.raises(ValueError, match="GPU"):
+            call()
+    for device in ("cpu", "meta"):
+        with pytest.raises(ValueError, match="GPU"):
+            bd._stream(torch.device(device))
