@@ -60,8 +60,11 @@ struct FwdCfg {
   // 128 heads).  A tile's V is read one 64-key unit later than its K, so with
   // one unit per tile V takes a third buffer.
   static constexpr int BK = 2 * (k_bytes(128) + v_bytes(128)) * WGS <= 158 * 1024 ? 128 : 64;
-  // MFMAs that an LDS operand is read ahead of its own (d = 128: two spilled, 0.744 against 0.734 ms)
-  static constexpr int AHEAD = DQK == 128 ? 1 : 2;
+  // MFMAs that an LDS operand is read ahead of its own.  With dv = 128 two
+  // spill: 0.744 against 0.734 ms at d = 128; at 192 / 128 242 against 238 us
+  // where two workgroups share a compute unit, 46.5 against 47.4 where one has it
+  // to itself, and with three isolated channels 357 against 292 us.
+  static constexpr int AHEAD = DV == 128 ? 1 : 2;
   static constexpr int U = BK / 64, NVB = U == 1 ? 3 : 2;
   // K part: row codes [BK][DQK], swizzled; row scales [BK][DQK/32]; isolated-channel key values [NH][BK] FP32
   static constexpr int KS_OFF = BK * DQK, KH_OFF = al16(KS_OFF + BK * DQK / 32), KST = KH_OFF + BK * 4 * NH;
@@ -172,9 +175,15 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
 
   // Loads of a tile: codes and K scales straight to LDS; the V col scales
   // (BK / 32 strided bytes per channel) and the isolated-channel bytes of
-  // each key through registers, written by finish_k() / finish_v().
+  // each key through registers, written by finish_k() / finish_v().  With
+  // three isolated channels and 64-key tiles thread 64 n + key takes channel n
+  // of that key (SPREAD); the first BK threads take all of theirs elsewhere.
+  // SPREAD saves four registers a lane where they spill (192 / 128, 2 x 4096
+  // tokens, causal: 258 against 292 us); 128-key tiles are up to 3 % slower so.
+  constexpr bool SPREAD = NH == 3 && U == 1;
+  constexpr int KH = SPREAD ? 1 : NH;
   uint32_t vsr[BK / 32] = {};
-  uint32_t khc[NH] = {}, khs[NH] = {};
+  uint32_t khc[KH] = {}, khs[KH] = {};
   RowLoads<DQK, NW, BK> kload;
   ColLoads<DV, NW, BK> vload;
   kload.init(w, lane);
@@ -183,7 +192,13 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
   auto issue_k = [&](lds8* st, int j0) __attribute__((always_inline)) {
     kload.issue(st, kcode, j0, L.k, w);
     dma_row_scales<DQK, NW, BK>(st + C::KS_OFF, kscale, j0, L.k, w, lane, 0);
-    if (hot >= 0 && threadIdx.x < BK) {
+    if constexpr (SPREAD) {
+      if (hot >= 0 && w < NH) {
+        const int r = j0 + lane < L.k ? j0 + lane : L.k - 1, ch = w == 0 ? hots[0] : w == 1 ? hots[1] : hots[NH - 1];
+        khc[0] = kcode[(int64_t)r * DQK + ch];
+        khs[0] = kscale[(int64_t)r * (DQK / 32) + ch / 32];
+      }
+    } else if (hot >= 0 && threadIdx.x < BK) {
       const int r = j0 + (int)threadIdx.x < L.k ? j0 + (int)threadIdx.x : L.k - 1;
 #pragma unroll
       for (int i = 0; i < NH; i++) {
@@ -203,7 +218,9 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
     }
   };
   auto finish_k = [&](uint8_t* st) __attribute__((always_inline)) {
-    if (threadIdx.x < BK) {
+    if constexpr (SPREAD) {
+      if (w < NH) reinterpret_cast<float*>(st + C::KH_OFF)[threadIdx.x] = hot >= 0 ? scaled_value(khc[0], khs[0]) : 0.f;
+    } else if (threadIdx.x < BK) {
 #pragma unroll
       for (int i = 0; i < NH; i++)
         reinterpret_cast<float*>(st + C::KH_OFF)[i * BK + threadIdx.x] = hot >= 0 ? scaled_value(khc[i], khs[i]) : 0.f;
