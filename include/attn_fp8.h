@@ -360,7 +360,8 @@ int attn_fp8_bwd_workspace_size(const attn_fp8_problem* p, size_t* bytes);
  *            gradients are bitwise those of the plain one).
  *   main_events nullable pointer to two events: recorded on `stream`
  *            immediately before and after the main backward kernel, so a
- *            caller can time that kernel alone. */
+ *            caller can time that kernel alone (with split query tiles the
+ *            pass that adds up and writes dV and dK follows the second). */
 int attn_fp8_bwd(const attn_fp8_problem* p, int delta_mode, const attn_fp8_mx* q,
                  const attn_fp8_mx* k, const attn_fp8_mx* v, const attn_fp8_mx* dout,
                  const float* lse, const void* dout_raw, int dout_dtype,
@@ -399,15 +400,17 @@ int attn_fp8_bwd_protected_dp(const attn_fp8_problem* p, const attn_fp8_mx* q,
 
 /* Backward without any device allocation, for callers that cannot allocate
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * allocation).  Same arguments, checks and results as attn_fp8_bwd, whose
- * kernels it runs, except that the workspace is the library's own scratch:
+ * allocation).  Same arguments, checks and results as attn_fp8_bwd on a
+ * workspace of the scratch's size, whose kernels it runs; the workspace is the
+ * library's own scratch:
  * ATTN_FP8_NOALLOC_SCRATCH_BYTES of device memory per device, held from the
  * call that first uses a device until the process ends (its device address
  * is looked up once per device with that device current).
  *   - Problems whose workspace without partial sums (see
  *     attn_fp8_bwd_workspace_size) exceeds the scratch are rejected with
  *     ATTN_FP8_EUNSUPPORTED before anything is launched; one that fits only
- *     without them runs unsplit.
+ *     without them runs unsplit: dK and dV are then those of attn_fp8_bwd with
+ *     a full workspace to FP32 rounding of their sums, dQ bit for bit.
  *   - The call allocates and frees nothing (no hipMalloc/hipFree, no
  *     allocating library routine).
  *   - All calls on one device share its scratch and leave their contents

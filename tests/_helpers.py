@@ -166,3 +166,14 @@ def check_row_stat_fields(gpu_rs, orc_rs):
         live = o > 0
         out[name] = float(np.median(np.abs(g[live] - o[live]) / o[live])) if live.any() else 0.0
     return out
+
+
+def unsplit_bytes(p):
+    """Workspace bytes of the backward of p without partial sums (the layout the header states)."""
+    r = lambda x: (x + 255) // 256 * 256
+    nqt, nkt, H = (p.seqlen + 63) // 64, (p.nk + 63) // 64, p.batch * p.heads_q
+    units = sum(q // 2 + 1 for q in range(p.seqlen // 32)) if p.causal else p.seqlen // 32 * nkt
+    D = p.dim_qk + p.dim_v
+    extra = r(2 * H * p.seqlen * p.dim_v) + r(2 * p.batch * p.heads_kv * p.nk * p.dim_v) if p.flags & pk.FLAG_PROTECTED_DP else 0
+    return (r(H * units * 2048) + r(H * units * 2) + r(H * p.seqlen * 8) + r(H * nqt * 1024) + r(H * nqt * 2 * D) +
+            r(p.batch * p.heads_kv * nkt * 2 * p.dim_qk) + extra)

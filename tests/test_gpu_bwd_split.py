@@ -8,18 +8,9 @@ import pytest
 import torch
 
 import paper_2609_37852_amd as pk
+from _helpers import unsplit_bytes
 
 pytestmark = pytest.mark.gpu
-
-
-def _unsplit_bytes(p):
-    r = lambda x: (x + 255) // 256 * 256
-    nqt, nkt, H = (p.seqlen + 63) // 64, (p.nk + 63) // 64, p.batch * p.heads_q
-    units = sum(q // 2 + 1 for q in range(p.seqlen // 32)) if p.causal else p.seqlen // 32 * nkt
-    D = p.dim_qk + p.dim_v
-    extra = r(2 * H * p.seqlen * p.dim_v) + r(2 * p.batch * p.heads_kv * p.nk * p.dim_v) if p.flags & pk.FLAG_PROTECTED_DP else 0
-    return (r(H * units * 2048) + r(H * units * 2) + r(H * p.seqlen * 8) + r(H * nqt * 1024) + r(H * nqt * 2 * D) +
-            r(p.batch * p.heads_kv * nkt * 2 * p.dim_qk) + extra)
 
 
 @pytest.mark.parametrize("B,N,Nk,Hq,Hkv,dqk,dv,causal,flags,lens", [
@@ -45,7 +36,7 @@ def test_split_equals_unsplit(B, N, Nk, Hq, Hkv, dqk, dv, causal, flags, lens, d
                    seqlen_kv=0 if causal else Nk, flags=flags, seqlens_q=L)
     mq, mk, mv, mdo = (pk.attn_fp8_quantize(t) for t in (q, k, v, do))
     o, lse = pk.attn_fp8_fwd(p, mq, mk, mv, lse=torch.zeros((B, Hq, N), device="cuda"), o=torch.zeros_like(do))
-    need, base = pk.attn_fp8_bwd_workspace_size(p), _unsplit_bytes(p)
+    need, base = pk.attn_fp8_bwd_workspace_size(p), unsplit_bytes(p)
     assert need > base, "this problem is not split"
 
     def run(nbytes, rowstats=False):

@@ -3,15 +3,15 @@ two calls in a row on one device, the second with a smaller problem, each
 against attn_fp8_bwd with a caller workspace (bitwise: the same kernels) and,
 with the matched correction, against the oracle (relative Frobenius error
 <= 2e-2); padded batches without the mask (sequences of their own lengths)
-bitwise equal as well; a problem whose scratch need exceeds the library's
-scratch is rejected before any launch."""
+bitwise equal as well; a problem whose partial sums alone exceed the library's
+scratch runs unsplit, one whose other needs do is rejected before any launch."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2609_37852_amd as pk
 from paper_2609_37852_amd import synth
-from _helpers import REL_TOL, np64, problem, rel_err, run_oracle, say, to_dev
+from _helpers import REL_TOL, np64, problem, rel_err, run_oracle, say, to_dev, unsplit_bytes
 
 pytestmark = pytest.mark.gpu
 
@@ -75,6 +75,28 @@ def test_noalloc_varlen_unmasked():
         torch.cuda.synchronize()
         for name, a, b in zip(("dQ", "dK", "dV"), na[:3], ws[:3]):
             assert torch.equal(a.view(torch.int32), b.view(torch.int32)), (i, name)
+
+
+def test_noalloc_without_room_for_partial_sums():
+    """A problem that the workspace backward splits and whose partial sums do
+    not fit the scratch: bitwise the backward on a workspace without them, and
+    the split one to the rounding of the FP32 sums of dK and dV."""
+    w = synth.with_shape(synth.WORKLOADS["gqa_d256_8k_qknorm"], B=1, N=2048, Hq=8, Hkv=2)
+    p = problem(w)
+    need, base = pk.attn_fp8_bwd_workspace_size(p), unsplit_bytes(p)
+    assert base <= pk.binding.NOALLOC_SCRATCH_BYTES < need
+    _, (mq, mk, mv, mdo), lse, do, o = _inputs(w, seed=30)
+
+    def run(f, **kw):
+        return f(p, pk.DELTA_MATCHING, mq, mk, mv, mdo, lse, do, o, grad_dtype=torch.float32, **kw)[:3]
+
+    na = run(pk.attn_fp8_bwd_noalloc)
+    one, split = (run(pk.attn_fp8_bwd, workspace=torch.empty(n, dtype=torch.uint8, device="cuda")) for n in (base, need))
+    for name, a, b, c in zip(("dQ", "dK", "dV"), na, one, split):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32)), name
+        # dK, dV: 4 heads x 32 query tiles of FP32 additions regrouped, 2^-24 of the largest partial sum each
+        assert rel_err(np64(a), np64(c)) <= (0.0 if name == "dQ" else 128 * 2.0 ** -24), name
+    assert not torch.equal(one[1], split[1])          # the split was taken
 
 
 def test_noalloc_rejects_problems_beyond_its_scratch():
