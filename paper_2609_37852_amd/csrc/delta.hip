@@ -429,9 +429,8 @@ static hipError_t delta_dispatch(const AttnArgs& a, hipStream_t s) {
   if constexpr (DQK != 192) {
     using C2 = DeltaCfg<DQK, DV, 1, true, 2>;
     const int64_t wgs = (a.N + C2::BQ - 1) / C2::BQ * a.Hq * a.B;
-    const int cus = cu_count();
-    if (cus <= 0) return hipErrorInvalidDevice;
-    if (wgs >= (int64_t)2 * cus * C2::WGS) return delta_launch<DQK, DV, 2>(a, s);
+    const int cus = cu_count();   // 0 if unknown
+    if (cus > 0 && wgs >= (int64_t)2 * cus * C2::WGS) return delta_launch<DQK, DV, 2>(a, s);
   }
   return delta_launch<DQK, DV, 1>(a, s);
 }
