@@ -17,38 +17,37 @@
 
 namespace afp8 {
 
-// Sixteen channels of a token.  NT (the plain quantizer): non-temporal loads,
-// since the input is read once and the caches are better left to the codes
-// being written, which the attention kernels read next (both copies of 134 MB
-// of BF16: 62.8 us with plain loads, 58.7 so).  The producer's quantizer reads
-// what its other passes have just read, so there the loads are plain (67
-// against 68 us for the key of 4 x 8192 tokens).
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
+// Sixteen channels of a token.  Plain loads: a lane's 32 or 64 bytes take two
+// or four instructions, which share cache lines with each other and with the
+// neighbour's.  Non-temporal ones (plain / non-temporal, us): FP32 67 MB 22 / 33,
+// 268 MB 86 / 111; BF16 34 MB 18.1 / 22.7, 101 MB 45.7 / 50.0, 134 MB 58 / 63
+// (66 / 62 when the same input is read over and over), 268 MB 166 / 142; the four
+// operands of a step (BF16, 16 / 4 heads of 128) of 2 x 8192 tokens 92 / 89,
+// 4 x 8192 168 / 172, 8 x 8192 307 / 322, FP32 4 x 4096 122 / 151.
+template <typename T>
+__device__ __forceinline__ void load16(const T* p, float (&v)[16]);
 
-template <bool NT>
-__device__ __forceinline__ v4u load_v4(const v4u* p) {
-  if constexpr (NT) return __builtin_nontemporal_load(p);
-  else return *p;
+template <>
+__device__ __forceinline__ void load16<float>(const float* p, float (&v)[16]) {
+  const float4* q = reinterpret_cast<const float4*>(p);
+#pragma unroll
+  for (int k = 0; k < 4; k++) {
+    float4 f = q[k];
+    v[4 * k] = f.x; v[4 * k + 1] = f.y; v[4 * k + 2] = f.z; v[4 * k + 3] = f.w;
+  }
 }
-template <typename T, bool NT>
-__device__ __forceinline__ void load16(const T* p, float (&v)[16]) {
-  const v4u* q = reinterpret_cast<const v4u*>(p);
-  if constexpr (sizeof(T) == 4) {
+
+template <>
+__device__ __forceinline__ void load16<uint16_t>(const uint16_t* p, float (&v)[16]) {
+  const uint4* q = reinterpret_cast<const uint4*>(p);
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-      const v4u u = load_v4<NT>(q + k);
+  for (int k = 0; k < 2; k++) {
+    uint4 u = q[k];
+    uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
-      for (int m = 0; m < 4; m++) v[4 * k + m] = __uint_as_float(u[m]);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 2; k++) {
-      const v4u u = load_v4<NT>(q + k);
-#pragma unroll
-      for (int m = 0; m < 4; m++) {
-        v[8 * k + 2 * m] = __uint_as_float(u[m] << 16);
-        v[8 * k + 2 * m + 1] = __uint_as_float(u[m] & 0xffff0000u);
-      }
+    for (int m = 0; m < 4; m++) {
+      v[8 * k + 2 * m] = __uint_as_float(w[m] << 16);
+      v[8 * k + 2 * m + 1] = __uint_as_float(w[m] & 0xffff0000u);
     }
   }
 }
@@ -148,7 +147,7 @@ __global__ __launch_bounds__(2 * D) void quantize_kernel(QuantArgs a) {
   float v[NB][16];
 #pragma unroll
   for (int u = 0; u < NB; u++) {
-    if (u < nb) load16<T, !PROD>(src + (n0 + 32 * u + tok) * a.sn, v[u]);
+    if (u < nb) load16<T>(src + (n0 + 32 * u + tok) * a.sn, v[u]);
     else {
 #pragma unroll
       for (int k = 0; k < 16; k++) v[u][k] = 0.f;
