@@ -366,14 +366,15 @@ hipError_t launch_bwd_reduce(const AttnArgs& a, int dqk, int dv, hipStream_t s) 
 // so a problem with few key blocks leaves compute units idle while its longest
 // block runs.  Splitting the tiles into n parts shortens that to 1 / n, at the
 // price of n FP32 partial sums written and read again and one more launch.
-// The model, for the 256 compute units of the whole chip: a tile step takes
+// The model, for the 256 compute units of a whole chip whatever device is
+// current (the workspace size and the sums depend on the problem alone): a tile step takes
 // 1.75 us at dqk + dv = 256 (scaled with it); without the mask all parts are
 // alike and run in rounds of one per compute unit, under it the launch ends no
 // sooner than its longest part and than its steps spread evenly; partial sums
 // move at 4 TB/s; the added launch and its pass take 8 us.  Backward call unsplit / split, 16 / 4
-// heads of 128, one sequence, causal: 512 tokens 76 / 43 us, 1024 128 / 55,
-// 2080 243 / 117, 4096 445 / 204, 8192 918 / 631; d = 256, 8 / 2 heads, 2048
-// tokens 320 / 128; 4 x 8192 tokens are not split.
+// heads of 128, one sequence, causal: 512 tokens 75 / 43 us, 1024 127 / 56,
+// 2080 241 / 116, 4096 440 / 197, 8192 908 / 601; d = 256, 8 / 2 heads, 2048
+// tokens 308 / 123; 4 x 8192 tokens are not split.
 int bwd_split(int64_t B, int64_t N, int64_t Nk, int64_t Hq, int64_t Hkv, int dqk, int dv, bool causal) {
   constexpr int64_t CUS = 256;
   const int64_t bkb = dqk + dv > 256 ? 64 : 128, nkb = (Nk + bkb - 1) / bkb, nqt = (N + 63) / 64, G = Hq / Hkv;
@@ -428,7 +429,7 @@ static hipError_t bwd_dispatch(const AttnArgs& a0, hipStream_t s) {
   const int64_t nkb = (a0.Nk + C::BKB - 1) / C::BKB;
   const dim3 grid((unsigned)(nkb * a0.Hkv * a0.B * a0.nsplit));
   // workgroups of one KV head and part that run at once: one per compute unit
-  // (the kernel's LDS allows one), the units shared by the B Hkv heads
+  // (its LDS allows one; at d = 64 its registers do), the units shared by the B Hkv heads
   const int cus = cu_count();
   if (cus <= 0) return hipErrorInvalidDevice;
   AttnArgs a = a0;

@@ -34,7 +34,7 @@ namespace afp8 {
 
 // QB: 32-query blocks per wave (2: every K / V fragment read from LDS serves
 // two blocks).
-template <int DQK, int DV, int NH = 1, bool CAUSAL = true, int QB_ = 1>
+template <int DQK, int DV, int NH = 1, int QB_ = 1>
 struct DeltaCfg {
   // 192 / 128 heads take 64-key tiles, so that two double-buffered workgroups
   // fit a CU; dv = 256 keeps 128-key tiles and one workgroup, since two do not
@@ -74,8 +74,8 @@ struct DeltaCfg {
 // FP64 products and sums; NH: isolated score channels (with 3, channels 1
 // and 2 take a second rank-2 FP32 MFMA, the first shares one with the shift)
 template <int DQK, int DV, bool CAUSAL, bool COMP, int NH, int QB>
-__global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void delta_matching_kernel(AttnArgs a) {
-  using C = DeltaCfg<DQK, DV, NH, CAUSAL, QB>;
+__global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, QB>::WGS)) void delta_matching_kernel(AttnArgs a) {
+  using C = DeltaCfg<DQK, DV, NH, QB>;
   constexpr int NW = C::NW, BQ = C::BQ, BK = C::BK, NG = BK / 32;
   constexpr int KS = DQK / 64, VS = DV / 64;
   __shared__ __attribute__((aligned(16))) uint8_t stA[C::STAGE];
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(256, (DeltaCfg<DQK, DV, NH, CAUSAL, QB>::WGS)) void
 
 template <int DQK, int DV, int QB>
 static hipError_t delta_launch(const AttnArgs& a, hipStream_t s) {
-  using C = DeltaCfg<DQK, DV, 1, true, QB>;
+  using C = DeltaCfg<DQK, DV, 1, QB>;
   const int64_t nqb = (a.N + C::BQ - 1) / C::BQ;
   const dim3 grid((unsigned)(nqb * a.Hq * a.B));
   if (a.iso3) {
@@ -427,7 +427,7 @@ static hipError_t delta_launch(const AttnArgs& a, hipStream_t s) {
 template <int DQK, int DV>
 static hipError_t delta_dispatch(const AttnArgs& a, hipStream_t s) {
   if constexpr (DQK != 192) {
-    using C2 = DeltaCfg<DQK, DV, 1, true, 2>;
+    using C2 = DeltaCfg<DQK, DV, 1, 2>;
     const int64_t wgs = (a.N + C2::BQ - 1) / C2::BQ * a.Hq * a.B;
     const int cus = cu_count();   // 0 if unknown
     if (cus > 0 && wgs >= (int64_t)2 * cus * C2::WGS) return delta_launch<DQK, DV, 2>(a, s);

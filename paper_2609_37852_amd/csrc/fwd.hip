@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
   // j / 8): p = 2^(x - M), its sum, the codes C8(p / 2^E), the sums and casts
   // LAG pairs after the exponentials; then the natural key order (lane half
   // hf: keys 16 hf .. 16 hf + 15 of the group).
-  constexpr int LAG = 2, NITEM = 16 + LAG + 1;
+  constexpr int LAG = 2, NITEM = 16 + LAG;
   float p[32];
   int cd[8];
   auto item = [&](int i, const v16f (&s)[2]) __attribute__((always_inline)) {
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
       __builtin_amdgcn_sched_barrier(0);
       if (m + AH < NO) o[(m + AH) % (AH + 1)] = load(m + AH, Kt, hk, Vt, hv);
 #pragma unroll
-      for (int i = m * (NITEM - 1) / NO; i < (m + 1) * (NITEM - 1) / NO; i++) item(i, si);
+      for (int i = m * NITEM / NO; i < (m + 1) * NITEM / NO; i++) item(i, si);
       __builtin_amdgcn_sched_barrier(0);
     }
     order();
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
     }
     maxima(s0);
 #pragma unroll
-    for (int i = 0; i < NITEM - 1; i++) item(i, s0);
+    for (int i = 0; i < NITEM; i++) item(i, s0);
     order();
     pfr = npfr;
     psc = ne;
