@@ -285,10 +285,14 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
   // Vector work of a unit, first part: group maxima, the reference M, the
   // group exponents.  A lane holds 16 keys (8 (r/4) + 4 hf + r % 4) of each
   // group of its query; after one exchange lanes of half g hold group g's
-  // maximum, and from there work on that group alone.
+  // maximum, and from there work on that group alone.  O is rescaled by
+  // rescale(), once the codes of the unit before are in it: their scale byte
+  // cannot take a factor below its range.
   float nM;           // -M
   float sc2[2];       // 2^E of the two groups
   int ne;             // scale byte of group hf (for the P V product of this unit)
+  bool raised;        // M was raised: by which factor O shrinks
+  float alpha;
   auto maxima = [&](const v16f (&s)[2]) __attribute__((always_inline)) {
     float gm[2];
 #pragma unroll
@@ -301,18 +305,13 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
     const float own = __builtin_fmaxf(pm.lo, pm.hi);     // raw score units
     // M is raised where some row's maximum exceeds it by 2^kLazyRescale (from
     // -inf at the first unit)
-    if (__any(own * c > M + kLazyRescale)) {
+    raised = __any(own * c > M + kLazyRescale);
+    if (raised) {
       const float mnew = __builtin_fmaxf(M, __builtin_ceilf(__builtin_fmaxf(own, partner(own)) * c));
       const float df = __builtin_fmaxf(M - mnew, -300.f);  // M is -inf at first
       const int d = (int)df;                              // 0 for lanes whose maximum did not move
-      const float alpha = d < -126 ? 0.f : exp2i(d);
+      alpha = d < -126 ? 0.f : exp2i(d);
       lsum *= alpha;
-#pragma unroll
-      for (int cb = 0; cb < CB; cb++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) oacc[cb][r] *= alpha;
-      // codes of the unit before, not yet in O
-      psc = psc + d < 0 ? 0 : psc + d;
       M = mnew;
     }
     nM = -M;
@@ -323,6 +322,13 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
     const auto ee = __builtin_amdgcn_permlane32_swap((uint32_t)e, (uint32_t)e, false, false);
     sc2[0] = exp2i((int)ee[0]);
     sc2[1] = exp2i((int)ee[1]);
+  };
+  auto rescale = [&]() __attribute__((always_inline)) {
+    if (!raised) return;
+#pragma unroll
+    for (int cb = 0; cb < CB; cb++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) oacc[cb][r] *= alpha;
   };
   // Second part, in pairs of elements (pair j: elements 2 j, 2 j + 1 of group
   // j / 8): p = 2^(x - M), its sum, the codes C8(p / 2^E), the sums and casts
@@ -376,6 +382,7 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
       for (int i = m * NITEM / NO; i < (m + 1) * NITEM / NO; i++) item(i, si);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (!decltype(first_tag)::value) rescale();
     order();
     pfr = npfr;
     psc = ne;
@@ -441,6 +448,7 @@ __global__ __launch_bounds__(256, (FwdCfg<DQK, DV, NH>::WGS)) void fwd_kernel(At
       for (int r = 0; r < 16; r++) s0[g][r] = 8 * (r >> 2) + (r & 3) > lim ? -__builtin_inff() : s0[g][r];
     }
     maxima(s0);
+    rescale();
 #pragma unroll
     for (int i = 0; i < NITEM; i++) item(i, s0);
     order();

@@ -39,3 +39,28 @@ def test_forward_tiles(recipe, N, Nk, causal, rise):
     assert rel_err(np64(o), ref["O"]) <= REL_TOL
     check_blocks({"O": block_errors(np64(o), ref["O"])})
     assert np.max(np.abs(np64(lse) - ref["LSE"])) <= 1e-3 * max(1.0, float(np.max(np.abs(ref["LSE"]))))
+
+
+# Rows whose maximum jumps by 2^J after `early` keys of score 0: V of the early keys is 2^100 in half the channels, of
+# the later ones 1 in the others, so O shows the early weights 2^-J itself.  Exact in the codes (score J, weights of
+# the early groups 2^-8 * 256, V); FP32 holds weights down to 2^-126 of the running maximum, and smaller ones are 0.
+@pytest.mark.parametrize("dqk,dv", [(64, 64), (128, 128), (192, 128), (256, 256)])
+@pytest.mark.parametrize("early,J", [(64, 104), (64, 120), (64, 128), (128, 120), (128, 208), (192, 128), (256, 120), (256, 144)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_forward_far_jump(dqk, dv, early, J, causal):
+    N = 512
+    q, k, v = torch.zeros(1, N, 1, dqk), torch.zeros(1, N, 1, dqk), torch.zeros(1, N, 1, dv)
+    q[..., 0], k[:, early:, :, 0] = 1.0, float(J)
+    v[:, :early, :, :dv // 2], v[:, early:, :, dv // 2:] = 2.0 ** 100, 1.0
+    p = pk.Problem(1, N, 1, 1, dqk, dv, float(np.float32(np.log(2.0))), causal=int(causal), seqlen_kv=0 if causal else N)
+    o, lse = pk.attn_fp8_fwd(p, *(pk.attn_fp8_quantize(t.cuda()) for t in (q, k, v)), o_dtype=torch.float32)
+    o, lse = np64(o)[0, :, 0], np64(lse)[0, 0]
+    late = np.arange(N) - early + 1 if causal else np.full(N, N - early)      # later keys each query sees
+    i = late > 0
+    w = early * 2.0 ** -J / late[i]                                           # weight of all early keys
+    low, high = o[i, :dv // 2], o[i, dv // 2:]
+    rel = 4 * 2.0 ** -23                                                      # l's reciprocal and the product; the rest is exact
+    flushed = early * 2.0 ** -126 / late[i] if J > 126 else 0.0               # weights below FP32's range are 0
+    assert np.all(np.abs(low * 2.0 ** -100 - w[:, None]) <= (rel * w + flushed)[:, None])
+    assert np.all(np.abs(high - 1.0) <= rel)
+    assert np.all(np.abs(lse[i] - (J + np.log2(late[i])) * np.log(2.0)) <= 1e-4)

@@ -40,7 +40,7 @@ def _kernels():
 # kernel, template arguments in its mangled name, bytes of scratch a lane
 @pytest.mark.parametrize("pattern,limit", [
     (r"fwd_kernel\w*ELb[01]ELi1EE", 0),                       # one isolated channel
-    (r"fwd_kernel\w*ELb[01]ELi3EE", 64),                      # three: 192 / 128; d = 256 causal
+    (r"fwd_kernel\w*ELb[01]ELi3EE", 32),                      # three: 192 / 128
     (r"delta_matching_kernel\w*ELb[01]ELb[01]ELi[13]ELi1EE", 0),
     (r"delta_matching_kernel\w*ELb[01]ELb[01]ELi[13]ELi2EE", 32),   # two query blocks per wave, d = 128: outside its loops
     (r"bwd_kernelILi\d+ELi\d+ELb0E", 0),                      # without row statistics
