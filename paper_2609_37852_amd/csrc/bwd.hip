@@ -374,7 +374,9 @@ hipError_t launch_bwd_reduce(const AttnArgs& a, int dqk, int dv, hipStream_t s) 
 // move at 4 TB/s; the added launch and its pass take 8 us.  Backward call unsplit / split, 16 / 4
 // heads of 128, one sequence, causal: 512 tokens 75 / 43 us, 1024 127 / 56,
 // 2080 241 / 116, 4096 440 / 197, 8192 908 / 601; d = 256, 8 / 2 heads, 2048
-// tokens 308 / 123; 4 x 8192 tokens are not split.
+// tokens 308 / 123; 4 x 8192 tokens are not split.  A padded batch that is
+// nearly all padding loses the launch: four sequences of 64 tokens, padded to
+// 2048, 31.6 / 34.9.
 int bwd_split(int64_t B, int64_t N, int64_t Nk, int64_t Hq, int64_t Hkv, int dqk, int dv, bool causal) {
   constexpr int64_t CUS = 256;
   const int64_t bkb = dqk + dv > 256 ? 64 : 128, nkb = (Nk + bkb - 1) / bkb, nqt = (N + 63) / 64, G = Hq / Hkv;

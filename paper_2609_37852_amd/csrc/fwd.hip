@@ -81,11 +81,11 @@ struct FwdCfg {
 // the P V product of unit i - 1 and the vector work of unit i between them: a
 // wave issues in order, so vector work placed after a run of MFMAs would wait
 // until the last of them has issued, 64 cycles each.  Each MFMA's operands
-// are read from LDS one or two MFMAs ahead.  Bound: vector issue (busy 67 % of
+// are read from LDS one or two MFMAs ahead.  Bound: vector issue (busy 66 % of
 // the cycles: 4 of 4.6 instructions a pair are the method's own, half a
 // three-way max, the exponential and its fma, the sum, half a cast, of which
-// the exponential and the cast take two slots), the MFMA pipe 42 %, one or the
-// other 87 %.  On 4 x 8192 tokens, 16 / 4 heads, causal, d = 128: 0.838 ms with
+// the exponential and the cast take two slots), the MFMA pipe 41 %, one or the
+// other 86 %.  On 4 x 8192 tokens, 16 / 4 heads, causal, d = 128: 0.838 ms with
 // one unit's products and vector work after another, 0.732 so (d = 64 0.346 ->
 // 0.284 with 2 x 16 heads, d = 256 0.486 -> 0.369, 192 / 128 0.277 -> 0.249).
 //
